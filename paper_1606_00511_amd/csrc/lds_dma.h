@@ -15,11 +15,16 @@ namespace hfk {
 // MFMA, which serialises the fragment loads with the MFMAs.  The kernels
 // track these loads themselves (wait_vm before a stage is read).  M0 holds
 // the wave's LDS base and needs one wait state before the load.
-__device__ __forceinline__ void dma16(const void* src, void* dst) {
-  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
+__device__ __forceinline__ uint32_t lds_address(void* p) {
+  return __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p);
+}
+__device__ __forceinline__ void dma16_at(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(src), "s"(lds_addr) : "memory");
+}
+__device__ __forceinline__ void dma16(const void* src, void* dst) {
+  dma16_at(src, lds_address(dst));
 }
 
 // Wait until at most N vector-memory operations of this wave are pending
