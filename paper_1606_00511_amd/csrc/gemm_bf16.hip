@@ -25,7 +25,7 @@
 // within an XCD, walks groups of 8 tile rows column by column, so that the
 // workgroups resident at one time share their operand panels in L2.
 // K advances BK at a time through S stages of LDS, filled by direct
-// global-to-LDS loads (global_load_lds_dwordx4) issued S - 1 blocks ahead of
+// global-to-LDS loads (global_load_lds_dwordx4) issued S blocks ahead of
 // the block the MFMAs consume: no registers stage the operands, and each
 // wave waits only for the loads of the block it is about to read.
 // LDS tiles are [row][k]; the 16-byte chunks of a row are XOR-swizzled so
@@ -389,12 +389,11 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
   constexpr int NY = MODE == 0 ? 1 : 2;      // Y tiles per K block
   constexpr int STAGE = NX * TX::SIZE + NY * TY::SIZE;
   constexpr int LPB = NX * TX::INSTR + NY * TY::INSTR;   // loads per block per wave
-  static_assert(S >= 2 && (S - 2) * LPB < 64, "pipeline depth");
   __shared__ __attribute__((aligned(16))) bf16_t lds[S * STAGE];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / GN, wn = wave % GN;
   const int li = lane & 31, h = lane >> 5;
   int tn, tm, tz;
@@ -438,25 +437,26 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
   const bf16_t* const X1 = s.X[1];
   const bf16_t* const Y0 = s.Y[0];
   const bf16_t* const Y1 = s.Y[1];
-  // the direct loads of K block vb into stage st (X tiles, then Y tiles)
-  auto issue = [&](int vb, int st) {
-    const int seg = (MODE == 0) ? vb / kbps : 0;
+  // direct load j of K block vb into stage st (X tiles, then Y tiles)
+  const uint32_t lds0 = lds_address(lds);
+  auto issue1 = [&](int vb, int st, int j) {
+    const int seg = (MODE == 0 && vb >= kbps) ? 1 : 0;
     const int k0 = (vb - seg * kbps) * BK;
-    bf16_t* base = lds + st * STAGE;
-#pragma unroll
-    for (int t = 0; t < NX; ++t) {
+    const uint32_t base = lds0 + 2u * (uint32_t)(st * STAGE);
+    if (j < NX * TX::INSTR) {
+      const int t = j / TX::INSTR, i = j % TX::INSTR;
       const bf16_t* x = ((MODE == 0 ? seg : t) ? X1 : X0) + bx + k0;
-#pragma unroll
-      for (int j = 0; j < TX::INSTR; ++j)
-        dma16(x + offx[j], base + t * TX::SIZE + TX::dst(wave, j));
-    }
-#pragma unroll
-    for (int t = 0; t < NY; ++t) {
+      dma16_at(x + offx[i], base + 2u * (uint32_t)(t * TX::SIZE + TX::dst(wave, i)));
+    } else {
+      const int t = (j - NX * TX::INSTR) / TY::INSTR, i = (j - NX * TX::INSTR) % TY::INSTR;
       const bf16_t* y = ((MODE == 0 ? seg : t) ? Y1 : Y0) + by + k0;
-#pragma unroll
-      for (int j = 0; j < TY::INSTR; ++j)
-        dma16(y + offy[j], base + NX * TX::SIZE + t * TY::SIZE + TY::dst(wave, j));
+      dma16_at(y + offy[i],
+               base + 2u * (uint32_t)(NX * TX::SIZE + t * TY::SIZE + TY::dst(wave, i)));
     }
+  };
+  auto issue = [&](int vb, int st) {
+#pragma unroll
+    for (int j = 0; j < LPB; ++j) issue1(vb, st, j);
   };
   const int xrow = wm * 32 * WM + li;
   const int yrow = wn * 32 * WN + li;
@@ -495,18 +495,6 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
         }
       }
   };
-  auto compute = [&](int st) {
-    constexpr int NQ = BK / 16;
-    Frags fa, fb;
-    fetch(fa, st, 0);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if (q + 1 < NQ) fetch((q & 1) ? fa : fb, st, q + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mma((q & 1) ? fb : fa);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
 
   // bias sums: thread t owns row t % RM of the X tile and part t / RM of
   // its chunks
@@ -540,24 +528,36 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
     }
   };
 
-  // prologue: the first S - 1 blocks in flight
+  // The steps of a K block, and between the last two the change of stage:
+  // once every wave has the last step's fragments in registers, the block's
+  // stage takes the loads of the block S later, and the next block's first
+  // fragments are read while the last step's MFMAs run.  Changing at the
+  // block's end left the MFMAs idle from the barrier to the first fragments
+  // (speech net: G-N solve at 16,384 rows 14.36 -> 14.07 ms, fused exact
+  // product at 4,096 rows 1.91 -> 1.88 ms, bit-identical).
+  constexpr int NQ = BK / 16;
+  static_assert(NQ % 2 == 0 && (S - 1) * LPB < 64, "pipeline depth");
+  Frags fa, fb;
 #pragma unroll
-  for (int i = 0; i < S - 1; ++i)
+  for (int i = 0; i < S; ++i)
     if (i < nblk) issue(vb0 + i, i);
+  if (nblk > 0) {
+    // this wave's loads of block 0 have landed, then every wave's
+    if (nblk >= S) wait_vm<(S - 1) * LPB>();
+    else wait_vm<0>();
+    stage_barrier();
+    if (A0PF && a0pf && nblk == 1) a0_half(1);
+    fetch(fa, 0, 0);
+  }
   for (int it = 0; it < nblk; ++it) {
-    // this wave's loads of block it have landed once at most
-    // min(S - 2, nblk - 1 - it) later blocks are still pending
-    // (one unconditional wait, so that the compiler sees every earlier
-    // scalar and LDS operation complete on every path)
-    const int ahead = min(S - 2, nblk - 1 - it);
-    wait_vm<(S - 2) * LPB>();
-    if (S > 3 && ahead == 1) wait_vm<(S > 3 ? LPB : 0)>();
-    if (ahead == 0) wait_vm<0>();
-    stage_barrier();     // every wave's loads landed; stage it - 1 is free
-    if (it + S - 1 < nblk) issue(vb0 + it + S - 1, (it + S - 1) % S);
     const int st = it % S;
-    if (A0PF && a0pf && it == nblk - 1) a0_half(1 - st);
-    compute(st);
+#pragma unroll
+    for (int q = 0; q + 1 < NQ; ++q) {
+      fetch((q & 1) ? fa : fb, st, q + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mma((q & 1) ? fb : fa);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (BIAS && do_bias && vb0 + it < kbps) {
       const int row = tid % RM, part = tid / RM;
       constexpr int CPP = TX::CH / PARTS;
@@ -567,6 +567,24 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
       for (int cc = 0; cc < CPP; ++cc) t += chunk_sum<TX, BK>(lx0, row, part * CPP + cc);
       bsum += (double)t;
     }
+    if (it + 1 < nblk) {
+      // this wave's loads of block it + 1 have landed once at most
+      // min(S - 2, nblk - 2 - it) later blocks are still pending
+      // (one unconditional wait, so that the compiler sees every earlier
+      // scalar and LDS operation complete on every path)
+      const int ahead = min(S - 2, nblk - 2 - it);
+      wait_vm<(S - 2) * LPB>();
+      if (S > 3 && ahead == 1) wait_vm<(S > 3 ? LPB : 0)>();
+      if (S > 2 && ahead == 0) wait_vm<0>();
+      stage_barrier();     // every wave's loads landed; stage st is free
+      fetch(fa, (it + 1) % S, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (it + S < nblk) issue(vb0 + it + S, st);
+      else if (A0PF && a0pf && it == nblk - 2) a0_half(st);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mma(fb);
+    __builtin_amdgcn_sched_barrier(0);
   }
   if (BIAS && do_bias) {
     __shared__ double bpart2[RM];
