@@ -364,7 +364,7 @@ __device__ __forceinline__ void sgemm_body(const GemmShapeS& s, EpiArgs e) {
     };
 #pragma unroll
     for (int i = 0; i < S - 1; ++i)
-      if (i < nblk) issue(vb0 + i, i);
+      if (nblk > 0) issue(vb0 + min(i, nblk - 1), i);
     // blocks of the first segment, then, on its scale, those of the second
     const int n0blk = min(max(kbps - vb0, 0), nblk);
     steps(0, n0blk);
@@ -454,8 +454,11 @@ __device__ __forceinline__ void sgemm_body(const GemmShapeS& s, EpiArgs e) {
 }  // namespace
 
 // Two tile shapes: 256 x 256 on eight waves (each 128 x 64), one workgroup
-// per CU, and 128 x 128 on four waves (each 64 x 64), two per CU, where the
-// larger tiles leave CUs without one.
+// per CU, and 128 x 128 on four waves (each 64 x 64) where the larger tiles
+// leave CUs without one.  The smaller ones have two stages, so that two
+// workgroups fit a CU, or (t128d) as many as fill one CU's LDS, for grids that
+// give a CU one workgroup at most: nothing else covers its loads' latency
+// there.
 #define HF_SGEMM_KERNEL(NAME, EPI, YP)                                          \
   extern "C" __global__ __launch_bounds__(512, 2) void NAME##_t256(GemmShapeS s, \
                                                                    EpiArgs e) { \
@@ -464,6 +467,10 @@ __device__ __forceinline__ void sgemm_body(const GemmShapeS& s, EpiArgs e) {
   extern "C" __global__ __launch_bounds__(256, 2) void NAME##_t128(GemmShapeS s, \
                                                                    EpiArgs e) { \
     sgemm_body<EPI, YP, 4, 4, 2, 2, 2>(s, e);                                   \
+  }                                                                             \
+  extern "C" __global__ __launch_bounds__(256, 2) void NAME##_t128d(GemmShapeS s, \
+                                                                    EpiArgs e) { \
+    sgemm_body<EPI, YP, 4, 4, 2, 2, YP == 2 ? 4 : 3>(s, e);                     \
   }
 #define HF_SGEMM_ROWS(NAME, EPI)            \
   HF_SGEMM_KERNEL(NAME##2, EPI, 2)          \
@@ -796,9 +803,9 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 typedef void (*SKernel)(GemmShapeS, EpiArgs);
 struct SKernels {
-  SKernel t256, t128;
+  SKernel t256, t128, t128d;
 };
-#define HF_SKERNELS(NAME) SKernels{NAME##_t256, NAME##_t128}
+#define HF_SKERNELS(NAME) SKernels{NAME##_t256, NAME##_t128, NAME##_t128d}
 #define HF_SROWS(NAME) \
   (s.yplanes == 3 ? HF_SKERNELS(NAME##3) : HF_SKERNELS(NAME##2))
 
@@ -807,7 +814,11 @@ int launch(const Launch& L, const char* name, const SKernels& k, const GemmShape
            const EpiArgs& e, int ts, double flops, double bytes) {
   const dim3 grid(cdiv(s.N, ts), cdiv(s.M, ts), s.splits > 1 ? s.splits : 1);
   prof_begin(L, name);
-  hipExtLaunchKernelGGL(ts == 256 ? k.t256 : k.t128, grid, dim3(ts == 256 ? 512 : 256), 0,
+  // at most one workgroup per CU: the whole LDS goes into stages (speech net's
+  // G-N solve at 1,024 rows 10.72 -> 10.02 ms; with two workgroups per CU the
+  // two-stage form is the one that fits)
+  const bool deep = grid.x * grid.y * grid.z <= 256;
+  hipExtLaunchKernelGGL(ts == 256 ? k.t256 : deep ? k.t128d : k.t128, grid, dim3(ts == 256 ? 512 : 256), 0,
                         L.stream, prof_a(L), prof_b(L), 0, s, e);
   prof_end(L, name, flops, bytes);
   return (int)(grid.x * grid.y) * (ts == 256 ? 8 : 4);
