@@ -57,6 +57,9 @@ CASES = [
     ((1024, 1025, 1300), "tanh", 2100),
     ((784, 1500, 1501, 12), "relu", 2000),
     ((2200, 2100, 2050), "sigmoid", 512),
+    # the weight gradient's last split holds one K block, fewer than the
+    # stages of a grid with one workgroup per CU
+    ((256, 512, 10), "tanh", 16870),
 ]
 
 
