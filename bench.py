@@ -40,10 +40,7 @@ sys.path.insert(0, ROOT)
 METRIC = ("curvature-vector products/sec (Hv & Gv) at batch B; "
           "CG iteration ms; % MFMA peak")
 PEAK_FP32_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
-PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 (and fp16) matrix peak
-# fp32 GEMMs on fp16 pairs (hf_sgemm_*): three fp16 products per fp32 product
-PEAK_PAIRS_TFLOPS = PEAK_BF16_TFLOPS / 3
-GEMMS = ("hf_gemm", "hf_hgemm", "hf_sgemm")
+PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 matrix peak
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 DEFAULT_WORKLOAD = "speech_440_2048x4_1973_sigmoid_b16384"
 
@@ -78,14 +75,14 @@ def counter_traffic(kernel, workload):
     """HBM bytes per launch of `kernel` from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE summary, or None when the summary was taken on
     another workload, does not cover the kernel, or its GEMM source
-    (gemm.hip, gemm_bf16.hip for the bf16 kernels, gemm_split.hip for those on
-    fp16 pairs) has changed since the counters were taken."""
+    (gemm.hip, or gemm_bf16.hip for the bf16 kernels) has changed since the
+    counters were taken."""
     import hashlib
-    stem = ("gemm_bf16" if kernel.startswith("hf_hgemm") else
-            "gemm_split" if kernel.startswith("hf_sgemm") else "gemm")
+    bf16 = kernel.startswith("hf_hgemm")
     path = os.path.join(ROOT, "profiles", "speech_b16384_hbm_counters.md")
-    src = os.path.join(ROOT, "paper_1606_00511_amd", "csrc", stem + ".hip")
-    tag = stem + "_source_sha256"
+    src = os.path.join(ROOT, "paper_1606_00511_amd", "csrc",
+                       "gemm_bf16.hip" if bf16 else "gemm.hip")
+    tag = "gemm_bf16_source_sha256" if bf16 else "gemm_source_sha256"
     try:
         lines = open(path).read().split("\n")
         sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
@@ -211,7 +208,7 @@ def run_leg(args, w, inp, prec):
     torch.cuda.synchronize()
     breakdown = net.prof_stats()
     progress("profiled step done")
-    gemms = {k: st for k, st in breakdown.items() if k.startswith(GEMMS)}
+    gemms = {k: st for k, st in breakdown.items() if k.startswith(("hf_gemm", "hf_hgemm"))}
     dom = max(gemms, key=lambda k: gemms[k]["ms"])
     net.prof_reset()
     if args.timed_events == "none":
@@ -367,7 +364,7 @@ def summary(res, K, peak):
     ds = res["stats"][dom]
     achieved = ds["flops"] / (ds["ms"] * 1e-3) / 1e12
     stats = res["breakdown"]      # one step
-    gemms = {k: s for k, s in stats.items() if k.startswith(GEMMS)}
+    gemms = {k: s for k, s in stats.items() if k.startswith(("hf_gemm", "hf_hgemm"))}
     gemm_ms = sum(s["ms"] for s in gemms.values())
     gemm_fl = sum(s["flops"] for s in gemms.values())
     # the separate passes that complete split-K GEMMs (epilogue of the
@@ -434,9 +431,7 @@ def main():
         del src, dst
     K = args.steps
     r32 = run_leg(args, w, inp, "fp32")
-    peak32 = (PEAK_PAIRS_TFLOPS if r32["dom"].startswith("hf_sgemm")
-              else PEAK_FP32_TFLOPS)
-    s32 = summary(r32, K, peak32)
+    s32 = summary(r32, K, PEAK_FP32_TFLOPS)
     ds = s32["ds"]
     out = {
         "metric": METRIC,
@@ -459,8 +454,8 @@ def main():
         },
         "roofline": {
             "bound": "mfma", "kernel": s32["dom"],
-            "achieved": s32["achieved"], "peak": peak32,
-            "unit": "TFLOP/s", "frac": s32["achieved"] / peak32,
+            "achieved": s32["achieved"], "peak": PEAK_FP32_TFLOPS,
+            "unit": "TFLOP/s", "frac": s32["achieved"] / PEAK_FP32_TFLOPS,
             "traffic": counter_traffic(s32["dom"], w.name),
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "launches": ds["launches"], "avg_launch_ms": ds["ms"] / ds["launches"],

@@ -12,8 +12,7 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 HEADER = os.path.join(os.path.dirname(HERE), "include", "hf.h")
-SOURCES = ["hf_api.cpp", "gemm.hip", "gemm_bf16.hip", "gemm_split.hip",
-           "rowops.hip", "cgvec.hip",
+SOURCES = ["hf_api.cpp", "gemm.hip", "gemm_bf16.hip", "rowops.hip", "cgvec.hip",
            "noalloc.hip", "narrow.hip"]
 
 

@@ -48,7 +48,7 @@
 // the K sum identically for both operands.
 #include <type_traits>
 
-#include "epi.h"
+#include "act.h"
 #include "hf_internal.h"
 #include "lds_dma.h"
 
@@ -249,6 +249,90 @@ __device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
 __device__ __forceinline__ f32x16 mfma(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
+
+// ----------------------------------------------------------------- epilogues
+struct EFwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    const float z = v0 + e.bias[c];
+    e.out0[(size_t)r * e.ldo + c] = e.hidden ? act_f(e.act, z) : z;
+  }
+};
+struct EFwdRFwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float v1) {
+    const size_t o = (size_t)r * e.ldo + c;
+    const float z = v0 + e.bias[c];
+    const float rz = v1 + e.rbias[c];
+    if (e.hidden) {
+      const float a = act_f(e.act, z);
+      e.out0[o] = a;
+      e.out1[o] = rz;
+      e.out2[o] = act_d1(e.act, a) * rz;
+    } else {
+      e.out0[o] = z;
+      e.out1[o] = rz;
+    }
+  }
+};
+struct ERFwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    const size_t o = (size_t)r * e.ldo + c;
+    const float rz = v0 + e.rbias[c];
+    if (e.out1) e.out1[o] = rz;      // null: RZ not needed downstream
+    if (e.hidden) e.out2[o] = act_d1(e.act, e.aux0[(size_t)r * e.lda + c]) * rz;
+  }
+};
+struct EBwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    e.out0[(size_t)r * e.ldo + c] =
+        v0 * act_d1(e.act, e.aux0[(size_t)r * e.lda + c]);
+  }
+};
+// backward data that also caches E * phi''(A) for the Hessian product
+struct EBwdE2 {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    const size_t o = (size_t)r * e.ldo + c;
+    const float a = e.aux0[(size_t)r * e.lda + c];
+    e.out0[o] = v0 * act_d1(e.act, a);
+    e.out2[o] = v0 * act_d2(e.act, a);
+  }
+};
+struct EBwdRBwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float v1) {
+    const size_t o = (size_t)r * e.ldo + c;
+    const size_t ia = (size_t)r * e.lda + c;
+    const float a = e.aux0[ia];
+    const float d1 = act_d1(e.act, a);
+    e.out0[o] = v0 * d1;
+    e.out1[o] = v1 * d1 + v0 * act_d2(e.act, a) * e.aux1[ia];
+  }
+};
+struct ERBwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    const size_t ia = (size_t)r * e.lda + c;
+    e.out1[(size_t)r * e.ldo + c] =
+        v0 * act_d1(e.act, e.aux0[ia]) + e.aux2[ia] * e.aux1[ia];
+  }
+};
+struct EGNBwd {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    e.out1[(size_t)r * e.ldo + c] =
+        v0 * act_d1(e.act, e.aux0[(size_t)r * e.lda + c]);
+  }
+};
+struct EStore {
+  static __device__ __forceinline__ void apply(const EpiArgs& e, int r, int c,
+                                               float v0, float) {
+    e.out0[(size_t)blockIdx.z * e.split_stride + (size_t)r * e.ldo + c] = v0;
+  }
+};
 
 // ------------------------------------------------------------------- body
 // MODE 0: single (nseg K-segments, optional split-K over grid z)

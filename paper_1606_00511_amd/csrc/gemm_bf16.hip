@@ -37,7 +37,6 @@
 #include "act.h"
 #include "hf_internal.h"
 #include "lds_dma.h"
-#include "tile16.h"
 
 namespace hfk {
 namespace {
@@ -55,16 +54,48 @@ __device__ __forceinline__ bf16_t f2bf(float f) {
   return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 
-// sum of the 8 k values of chunk c of an LDS tile row
-template <class T, int BK>
-__device__ __forceinline__ float chunk_sum(const bf16_t* __restrict__ s, int row, int c) {
-  const u32x4 v = *(const u32x4*)(s + row * BK + ((c ^ T::swz(row)) * 8));
-  float t = 0.0f;
+// ------------------------------------------------------------ tile loading
+// A ROWS x BK tile kept in LDS as [row][k]; the CH 16-byte chunks of a row
+// are XOR-swizzled by (row / RPB) % CH, RPB being the number of rows that
+// span the 64 banks.  Chunk position P of the tile (P = row * CH + pos, 64
+// chunks per direct-load instruction) holds global chunk pos ^ swz(row).
+template <int ROWS, int BK, int NW>
+struct Tile {
+  static constexpr int CH = BK / 8;
+  static constexpr int RPB = 128 / BK;
+  static constexpr int SIZE = ROWS * BK;             // bf16 elements
+  static constexpr int INSTR = ROWS * CH / 64 / NW;  // direct loads per wave
+  static_assert(INSTR >= 1 && ROWS * CH % (64 * NW) == 0, "tile does not split over the waves");
+
+  __device__ static __forceinline__ int swz(int row) { return (row / RPB) % CH; }
+  // element offset, within an operand of leading dimension ld, of the chunk
+  // that lane `lane` of wave `wave` fetches with its instruction j
+  __device__ static __forceinline__ uint32_t src(int ld, int wave, int lane, int j) {
+    const int P = (wave * INSTR + j) * 64 + lane;
+    const int row = P / CH, pos = P % CH;
+    return (uint32_t)row * (uint32_t)ld + 8u * (uint32_t)(pos ^ swz(row));
+  }
+  // LDS element offset of the 64 chunks written by instruction j of a wave
+  __device__ static __forceinline__ int dst(int wave, int j) {
+    return (wave * INSTR + j) * 512;
+  }
+  // operand of MFMA step q (k = 16 q .. 16 q + 15) for lane (row, h)
+  __device__ static __forceinline__ bf16x8 frag(const bf16_t* __restrict__ s,
+                                                int row, int h, int q) {
+    const int c = 2 * q + h;
+    return *(const bf16x8*)(s + row * BK + ((c ^ swz(row)) * 8));
+  }
+  // sum of the 8 k values of chunk c of a row
+  __device__ static __forceinline__ float chunk_sum(const bf16_t* __restrict__ s,
+                                                    int row, int c) {
+    const u32x4 v = *(const u32x4*)(s + row * BK + ((c ^ swz(row)) * 8));
+    float t = 0.0f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    t += __uint_as_float(v[j] << 16) + __uint_as_float(v[j] & 0xffff0000u);
-  return t;
-}
+    for (int j = 0; j < 4; ++j)
+      t += __uint_as_float(v[j] << 16) + __uint_as_float(v[j] & 0xffff0000u);
+    return t;
+  }
+};
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -368,6 +399,27 @@ struct EStore {                      // fp32 only: never staged
   }
 };
 
+// ------------------------------------------------------------- tile order
+// The tile (tn, tm) and split tz this workgroup computes.  Linear dispatch
+// index L goes to XCD L % 8; when the grid is a multiple of 8, XCD x gets
+// the x-th contiguous eighth of the logical order.  Within a split, the
+// logical order walks groups of 8 tile rows, column by column.
+__device__ __forceinline__ void tile_of(int& tn, int& tm, int& tz) {
+  const int gx = gridDim.x, gy = gridDim.y;
+  const int T = gx * gy * gridDim.z;
+  const int L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const int Lg = (T % 8 == 0) ? (L % 8) * (T / 8) + L / 8 : L;
+  tz = Lg / (gx * gy);
+  const int r = Lg % (gx * gy);
+  constexpr int G = 8;
+  const int g = r / (G * gx);
+  const int first = g * G;
+  const int rows = min(G, gy - first);
+  const int w = r - g * G * gx;
+  tm = first + w % rows;
+  tn = w / rows;
+}
+
 // ------------------------------------------------------------------- body
 #ifndef HF_H_STAGE
 #define HF_H_STAGE 1
@@ -383,8 +435,8 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
   if (s.skip && *s.skip) return;
   constexpr int NW = GM * GN, NT = 64 * NW;
   constexpr int RM = 32 * WM * GM, RN = 32 * WN * GN;
-  using TX = Tile16<RM, BK, NW>;
-  using TY = Tile16<RN, BK, NW>;
+  using TX = Tile<RM, BK, NW>;
+  using TY = Tile<RN, BK, NW>;
   constexpr int NX = MODE == 1 ? 2 : 1;      // X tiles per K block
   constexpr int NY = MODE == 0 ? 1 : 2;      // Y tiles per K block
   constexpr int STAGE = NX * TX::SIZE + NY * TY::SIZE;
@@ -472,13 +524,13 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
     const bf16_t* ly1 = ly0 + (NY - 1) * TY::SIZE;
 #pragma unroll
     for (int a = 0; a < WM; ++a) {
-      f.x0[a] = TX::template frag<bf16x8>(lx0, xrow + 32 * a, h, q);
-      if (MODE == 1) f.x1[a] = TX::template frag<bf16x8>(lx1, xrow + 32 * a, h, q);
+      f.x0[a] = TX::frag(lx0, xrow + 32 * a, h, q);
+      if (MODE == 1) f.x1[a] = TX::frag(lx1, xrow + 32 * a, h, q);
     }
 #pragma unroll
     for (int b = 0; b < WN; ++b) {
-      f.y0[b] = TY::template frag<bf16x8>(ly0, yrow + 32 * b, h, q);
-      if (MODE != 0) f.y1[b] = TY::template frag<bf16x8>(ly1, yrow + 32 * b, h, q);
+      f.y0[b] = TY::frag(ly0, yrow + 32 * b, h, q);
+      if (MODE != 0) f.y1[b] = TY::frag(ly1, yrow + 32 * b, h, q);
     }
   };
   auto mma = [&](const Frags& f) {
@@ -564,7 +616,7 @@ __device__ __forceinline__ void hgemm_body(const GemmShapeH& s, const EpiH& e) {
       const bf16_t* lx0 = lds + st * STAGE;
       float t = 0.0f;
 #pragma unroll
-      for (int cc = 0; cc < CPP; ++cc) t += chunk_sum<TX, BK>(lx0, row, part * CPP + cc);
+      for (int cc = 0; cc < CPP; ++cc) t += TX::chunk_sum(lx0, row, part * CPP + cc);
       bsum += (double)t;
     }
     if (it + 1 < nblk) {

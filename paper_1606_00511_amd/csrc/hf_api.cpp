@@ -216,14 +216,6 @@ struct hf_ctx {
   size_t hbeg = 0, hend = 0;   // the bf16 region, zeroed by hf_set_workspace
   size_t hX = 0, hXT = 0;
   std::vector<size_t> hW, hWT, hV, hVT, hA, hAT, hRA, hRAT, hD, hDT, hRD, hRDT;
-  // fp32 contexts: fp16-pair GEMM operands (gemm_split.hip) of the layers in
-  // `pairs`; row-major copies have leading dimension ldp_l, the transposed
-  // ones *T ldBp (16-bit elements).  A[0] is the input X.
-  std::vector<char> pairs;
-  std::vector<int> ldp, ldw;   // ldw: weights contracted over d_l
-  int ldBp = 0;
-  std::vector<size_t> sW, sWT, sV, sVT, sA, sAT, sRA, sRAT, sD, sDT, sRD, sRDT;
-  size_t oSlot = 0, oCexp = 0, oAmax = 0, oWmax = 0, oCpart = 0, oBias = 0;
   size_t oS = 0, oT = 0, oRs = 0;    // Bi-CG-STAB: s, t = B s, r0*
   size_t oPh = 0, oSh = 0;           // preconditioned: M^-1 p, M^-1 s
   size_t oMv = 0;                    // hf_iterate's M^-1
@@ -291,12 +283,6 @@ struct hf_ctx {
   double* Dp(size_t off) const { return reinterpret_cast<double*>(ws + off); }
   bf16_t* H(size_t off) const { return reinterpret_cast<bf16_t*>(ws + off); }
   bool bf16() const { return prec == HF_BF16_INPUTS; }
-  // exponent slots: kind K_* of layer l
-  enum { K_W, K_V, K_A, K_RA, K_D, K_RD, K_COUNT };
-  int* slot(int kind, int l) const {
-    return reinterpret_cast<int*>(ws + oSlot) + kind * (HF_MAX_LAYERS + 1) + l;
-  }
-  uint32_t* U(size_t off) const { return reinterpret_cast<uint32_t*>(ws + off); }
   int* errp() const {
     return err_override ? err_override : reinterpret_cast<int*>(ws + oErr);
   }
@@ -330,36 +316,6 @@ inline bool a16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 inline int round4(int x) { return (x + 3) & ~3; }
 inline int round64(int x) { return (x + 63) & ~63; }
 inline size_t round256(size_t x) { return (x + 255) & ~size_t(255); }
-inline int round32(int x) { return (x + 31) & ~31; }
-
-// Planes of a weight operand contracted over K: a weight's value on pairs is
-// up to 2^-24 off, the same way for every row of the batch.  Over short
-// contractions that is more than the sums' own error, so the last bits go into
-// a third plane there (784-500x3-10 tanh net: error of G v against 64 bits
-// 7.9e-8 -> 4.7e-8, fp32 MFMAs 5.7e-8); above, the fp32 MFMAs' sums were
-// further off than either (440-1500x3-1000: 7.1e-7, pairs 1.9e-7).
-int planes_for(int K) { return K <= 1024 ? 3 : 2; }
-
-// Whether layer l's GEMMs run on fp16 pairs for B rows: where their shorter
-// time pays for the passes that split their operands.  Measured, loss /
-// gradient / G v / solve against the fp32 kernels: 1.1 to 1.3 times as fast at
-// 2.25e9 (300-1500x2-1000, 1,000 rows), 0.85 to 1.0 at 1.6e9 (784-200x2-10,
-// 10,000 rows; 784-500x2-40, 4,000 rows), 0.4 to 0.6 at 1e8.
-constexpr int PAIRS_MIN_WIDTH = 128;
-constexpr int64_t PAIRS_MIN_ROWS = 512;
-constexpr double PAIRS_MIN_WORK = 2.2e9;
-bool pairs_layer(const hf_ctx* c, int l, int64_t B) {
-  return c->d[l] >= PAIRS_MIN_WIDTH && c->d[l - 1] >= PAIRS_MIN_WIDTH && B >= PAIRS_MIN_ROWS &&
-         (double)B * c->d[l] * c->d[l - 1] >= PAIRS_MIN_WORK;
-}
-// Whether layer l's GEMMs (forward and R-forward into l, backward from l,
-// weight gradient of l) run on fp16 pairs for B rows.
-bool use_pairs(const hf_ctx* c, int l, int64_t B) { return c->pairs[l] && pairs_layer(c, l, B); }
-bool any_pairs(const hf_ctx* c, int64_t B) {
-  for (int l = 1; l <= c->L; ++l)
-    if (use_pairs(c, l, B)) return true;
-  return false;
-}
 
 // Carve the workspace for calls of up to B rows (B <= Bmax).  A
 // product-only layout holds what a stateless curvature product uses: no
@@ -418,55 +374,6 @@ void plan(hf_ctx* c, int64_t Bplan, bool product_only = false) {
       c->hRDT[l] = take(szt);
     }
     c->hend = off;
-  }
-  c->pairs.assign(L + 1, 0);
-  for (auto* v : {&c->sW, &c->sWT, &c->sV, &c->sVT, &c->sA, &c->sAT, &c->sRA, &c->sRAT,
-                  &c->sD, &c->sDT, &c->sRD, &c->sRDT})
-    v->assign(L + 1, 0);
-  if (!h && !product_only && Bplan >= PAIRS_MIN_ROWS) {
-    c->ldp.assign(L + 1, 0);
-    c->ldw.assign(L + 1, 0);
-    for (int l = 0; l <= L; ++l) {
-      c->ldp[l] = 2 * round32(c->d[l]);
-      c->ldw[l] = planes_for(c->d[l]) * round32(c->d[l]);
-    }
-    c->ldBp = 2 * round32((int)Bplan);
-    const size_t PB = round256(B);
-    bool any = false;
-    size_t parts = 4096;           // of the largest magnitudes of one tensor
-    for (int l = 1; l <= L; ++l) {
-      parts = std::max(parts, (B + 127) / 128 * (((size_t)c->d[l] + 127) / 128) * 4);
-      parts = std::max(parts, (B + 255) / 256 * (((size_t)c->d[l] + 255) / 256) * 8);
-      if (!pairs_layer(c, l, Bplan)) continue;
-      any = true;
-      c->pairs[l] = 1;
-      const size_t wrow = R256(c->d[l]) * c->ldw[l - 1] * h2;
-      c->sW[l] = take(wrow);
-      c->sV[l] = take(wrow);
-      const size_t arow = PB * c->ldp[l - 1] * h2, atr = R256(c->d[l - 1]) * c->ldBp * h2;
-      c->sA[l - 1] = take(arow);
-      c->sAT[l - 1] = take(atr);
-      c->sRDT[l] = take(R256(c->d[l]) * c->ldBp * h2);
-      c->sDT[l] = take(R256(c->d[l]) * c->ldBp * h2);
-      if (l == 1) continue;
-      const size_t wtr = R256(c->d[l - 1]) * c->ldw[l] * h2;
-      c->sWT[l] = take(wtr);
-      c->sVT[l] = take(wtr);
-      c->sRA[l - 1] = take(arow);
-      c->sRAT[l - 1] = take(atr);
-      c->sRD[l] = take(PB * c->ldp[l] * h2);
-      c->sD[l] = take(PB * c->ldp[l] * h2);
-    }
-    if (any) {
-      c->oSlot = take(hf_ctx::K_COUNT * (HF_MAX_LAYERS + 1) * sizeof(int));
-      c->oCexp = take((size_t)c->d[0] * sizeof(int));
-      c->oAmax = take(parts * sizeof(uint32_t));
-      c->oWmax = take((size_t)(L + 1) * SPLIT_WPARTS * sizeof(uint32_t));
-      c->oCpart = take((size_t)SPLIT_CPARTS * c->d[0] * sizeof(uint32_t));
-      int dm = 0;
-      for (int l = 1; l <= L; ++l) dm = std::max(dm, c->d[l]);
-      c->oBias = take((size_t)SPLIT_BPARTS * dm * sizeof(double));
-    }
   }
   for (int l = 1; l <= L; ++l) {
     const size_t sz = RB * c->ld[l] * f4;
@@ -644,35 +551,6 @@ int choose_splits(const hf_ctx* c, int M, int N, int Ktot) {
   return s;
 }
 
-// The same for the fp16-pair GEMMs: at most 4,096 rows per split (their sums
-// over 4,096 terms are closer to 64 bits than the fp32 MFMAs' over 2,048),
-// then 256 x 256 tiles on (nearly) every compute unit with at least 512 rows
-// each, or else 128 x 128 tiles with at least 128.
-int pair_splits(const hf_ctx* c, int M, int N, int Ktot) {
-  auto tiles = [&](int ts) { return (long long)((M + ts - 1) / ts) * ((N + ts - 1) / ts); };
-  int s = 1;
-  while (s < c->max_splits && (Ktot + s - 1) / s > 4096) s *= 2;
-  int t = s;
-  while (t < c->max_splits && split_tile(M, N, t) != 256 && Ktot / (2 * t) >= 512) t *= 2;
-  if (split_tile(M, N, t) == 256) s = t;
-  else
-    while (s < c->max_splits && tiles(128) * s < 256 && Ktot / (2 * s) >= 128) s *= 2;
-  while (s > 1 && (size_t)s * M * N > c->split_floats) s /= 2;
-  return s;
-}
-
-// Whether the weight gradient of delta_L uses pairs where its layer does.
-// delta_L is a softmax less a one-hot row, and an fp16 MFMA cuts the products
-// of 8 terms off 24 bits below the largest, which takes the low bits of a
-// class's many small probabilities away beside each label's -1; as their sums
-// nearly cancel, that shows.  The fp32 kernel is closer to 64 bits while its
-// splits are short (1021-203 layer, 3,001 rows in splits of 94: 8.6e-8, pairs
-// 1.5e-7), further off from splits of 256 rows (1500-1000 layer, 2,048 rows:
-// 9.6e-8, pairs 7.2e-8; 2048-1973, 512 rows a split: 4.3e-7, pairs 1.3e-7).
-bool pairs_delta_L(const hf_ctx* c, int B) {
-  return B / choose_splits(c, c->d[c->L], c->d[c->L - 1], B) >= 256;
-}
-
 GemmShape shape(int M, int N, int K, const float* x0, const float* x1,
                 const float* y0, const float* y1, int ldx, int ldy, int nseg,
                 const int* skip) {
@@ -697,119 +575,6 @@ EpiArgs epi(const hf_ctx* c, int hidden) {
   return e;
 }
 
-// ------------------------------------------------------ fp16-pair operands
-GemmShapeS shape_s(int M, int N, int K, int ldx, int ldy, const int* skip) {
-  GemmShapeS s;
-  std::memset(&s, 0, sizeof s);
-  s.M = M; s.N = N; s.K = K;
-  s.ldx = ldx; s.ldy = ldy;
-  s.nseg = 1;
-  s.splits = 1;
-  s.yplanes = 2;
-  s.skip = skip;
-  return s;
-}
-
-// one K-segment: pairs, exponent slots and fp32 sources
-void seg_s(const hf_ctx* c, GemmShapeS& s, int i, size_t x, const int* ex, const float* xf,
-           size_t y, const int* ey, const float* yf) {
-  s.nseg = i + 1;
-  s.X[i] = c->H(x);
-  s.ex[i] = ex;
-  s.Xf[i] = xf;
-  s.Y[i] = c->H(y);
-  s.ey[i] = ey;
-  s.Yf[i] = yf;
-}
-
-SplitJob split_job(const float* in, int R, int C, int ldi, int* slot) {
-  SplitJob j;
-  std::memset(&j, 0, sizeof j);
-  j.in = in;
-  j.R = R;
-  j.C = C;
-  j.ldi = ldi;
-  j.slot = slot;
-  j.prow = j.ptr = 2;
-  j.chunks = split_chunks(R, C);
-  return j;
-}
-
-// The pairs of a B x C tensor: row-major and / or transposed (offset 0: not
-// wanted).  namax: partials of its largest magnitudes already in oAmax; -1:
-// none yet, a pass of its own forms them.  bias: its column sums too, for the
-// weight gradient that comes next.
-void split_tensor(hf_ctx* c, const float* in, int B, int C, int ld, int ldp, size_t row,
-                  size_t tr, int* slot, int namax, const int* skip, bool bias = false) {
-  if (namax < 0) namax = absmax(c->launch(), in, B, C, ld, c->U(c->oAmax), skip);
-  SplitJobs js;
-  js.n = 1;
-  js.weights = 0;
-  js.j[0] = split_job(in, B, C, ld, slot);
-  js.j[0].row = row ? c->H(row) : nullptr;
-  js.j[0].ldr = ldp;
-  js.j[0].tr = tr ? c->H(tr) : nullptr;
-  js.j[0].ldt = c->ldBp;
-  js.j[0].amax = c->U(c->oAmax);
-  js.j[0].namax = namax;
-  js.j[0].bias = bias ? c->Dp(c->oBias) : nullptr;
-  split(c->launch(), js, skip);
-}
-
-// The pairs of the weight blocks of a parameter-layout vector (the layers
-// that use them at B rows): row-major, and transposed for the backward GEMMs
-// when wanted.
-void split_weights(hf_ctx* c, const float* v, int kind, int B, bool want_tr, const int* skip) {
-  const bool w = kind == hf_ctx::K_W;
-  SplitJobs js;
-  js.n = 0;
-  js.weights = 1;
-  for (int l = 1; l <= c->L; ++l) {
-    if (!use_pairs(c, l, B)) continue;
-    SplitJob& j = js.j[js.n++];
-    j = split_job(v + c->offW[l], c->d[l], c->d[l - 1], c->d[l - 1], c->slot(kind, l));
-    j.row = c->H(w ? c->sW[l] : c->sV[l]);
-    j.ldr = c->ldw[l - 1];
-    j.prow = planes_for(c->d[l - 1]);
-    j.tr = want_tr && l > 1 ? c->H(w ? c->sWT[l] : c->sVT[l]) : nullptr;
-    j.ldt = c->ldw[l];
-    j.ptr = planes_for(c->d[l]);
-    j.amax = c->U(c->oWmax) + (size_t)l * SPLIT_WPARTS;
-    j.namax = SPLIT_WPARTS;
-    j.cexp = l == 1 ? reinterpret_cast<int*>(c->ws + c->oCexp) : nullptr;
-  }
-  if (!js.n) return;
-  absmax_weights(c->launch(), js, skip);
-  split(c->launch(), js, skip);
-}
-
-// The pairs of the input X, each column scaled by its own exponent.
-void split_input(hf_ctx* c, const float* X, int B, bool want_tr) {
-  int* slot = c->slot(hf_ctx::K_A, 0);
-  const int parts =
-      absmax_columns(c->launch(), X, B, c->d[0], c->d[0], c->U(c->oCpart), slot);
-  SplitJobs js;
-  js.n = 1;
-  js.weights = 0;
-  js.j[0] = split_job(X, B, c->d[0], c->d[0], slot);
-  js.j[0].row = c->H(c->sA[0]);
-  js.j[0].ldr = c->ldp[0];
-  js.j[0].tr = want_tr ? c->H(c->sAT[0]) : nullptr;
-  js.j[0].ldt = c->ldBp;
-  js.j[0].cexp = reinterpret_cast<int*>(c->ws + c->oCexp);
-  js.j[0].cpart = c->U(c->oCpart);
-  js.j[0].namax = parts;
-  split(c->launch(), js, nullptr);
-}
-
-// Pairs of a tensor of layer l's output side once it is complete (offsets of
-// the row-major and transposed copies): only where the layer that reads it
-// (`reader`) uses pairs.  amax: where the producing GEMM puts its partials
-// (null: not needed).
-uint32_t* amax_for(hf_ctx* c, int reader, int B) {
-  return reader <= c->L && use_pairs(c, reader, B) ? c->U(c->oAmax) : nullptr;
-}
-
 // Weight-gradient GEMM into the parameter layout: out_W (d_l x d_{l-1}) =
 // sum_seg Xs^T Ys over the rows, and out_b = column sums of x0 (the first
 // segment's X operand), both from the same kernel.
@@ -819,41 +584,10 @@ void wgrad(hf_ctx* c, int l, int B, const float* x0, const float* y0,
   const Launch Lc = c->launch();
   const int M = c->d[l], N = c->d[l - 1];
   const int nseg = x1 ? 2 : 1;
-  EpiArgs e = epi(c, 0);
-  e.ldo = N;
-  // x0 is Rdelta_l or delta_l; y0 = A_{l-1}, x1 = delta_l, y1 = RA_{l-1}
-  const bool rd = x0 == c->F(c->oRD[l]);
-  if (!sq && use_pairs(c, l, B) && (rd || l < c->L || pairs_delta_L(c, B))) {
-    GemmShapeS s = shape_s(M, N, B, c->ldBp, c->ldBp, skip);
-    seg_s(c, s, 0, rd ? c->sRDT[l] : c->sDT[l], c->slot(rd ? hf_ctx::K_RD : hf_ctx::K_D, l),
-          x0, c->sAT[l - 1], c->slot(hf_ctx::K_A, l - 1), y0);
-    if (x1)
-      seg_s(c, s, 1, c->sDT[l], c->slot(hf_ctx::K_D, l), x1, c->sRAT[l - 1],
-            c->slot(hf_ctx::K_RA, l - 1), y1);
-    s.xr = 1;
-    s.xk = c->ld[l];
-    s.yr = 1;
-    s.yk = ldy;
-    s.yc = l == 1 ? reinterpret_cast<const int*>(c->ws + c->oCexp) : nullptr;
-    s.splits = pair_splits(c, M, N, B * nseg);
-    // the split of x0 left its column sums
-    const double* bias = c->Dp(c->oBias);
-    const int bparts = split_chunks(B, M);
-    if (s.splits > 1) {
-      e.out0 = c->F(c->oSplit);
-      e.split_stride = (long long)M * N;
-      sgemm_wgrad(Lc, s, e);
-      splitk_reduce(Lc, c->F(c->oSplit), bias, s.splits, M, N, out + c->offW[l], N,
-                    out + c->offB[l], skip, bparts);
-    } else {
-      e.out0 = out + c->offW[l];
-      sgemm_wgrad(Lc, s, e);
-      bias_sum(Lc, bias, bparts, M, out + c->offB[l], skip);
-    }
-    return;
-  }
   GemmShape s = shape(M, N, B, x0, x1, y0, y1, c->ld[l], ldy, nseg, skip);
   s.splits = choose_splits(c, M, N, B * nseg);
+  EpiArgs e = epi(c, 0);
+  e.ldo = N;
   if (s.splits > 1) {
     e.out0 = c->F(c->oSplit);
     e.split_stride = (long long)M * N;
@@ -870,15 +604,13 @@ void wgrad(hf_ctx* c, int l, int B, const float* x0, const float* y0,
 
 // Weight blocks of a parameter-layout vector, transposed to [d_{l-1}][ld_l]
 // (the row-contiguous right operand of the forward GEMMs).
-// Layers that use fp16 pairs at B rows have no use for it.
-void transpose_weights(hf_ctx* c, const float* v, const std::vector<size_t>& dst, int B,
+void transpose_weights(hf_ctx* c, const float* v, const std::vector<size_t>& dst,
                        const int* skip) {
   TransposeBatch b;
   static_assert(TransposeBatch::MAX >= HF_MAX_LAYERS, "one block per layer");
-  b.n = 0;
+  b.n = c->L;
   for (int l = 1; l <= c->L; ++l) {
-    if (use_pairs(c, l, B)) continue;
-    const int i = b.n++;
+    const int i = l - 1;
     b.in[i] = v + c->offW[l];
     b.R[i] = c->d[l];
     b.C[i] = c->d[l - 1];
@@ -886,88 +618,44 @@ void transpose_weights(hf_ctx* c, const float* v, const std::vector<size_t>& dst
     b.out[i] = c->F(dst[l]);
     b.ldo[i] = c->ld[l];
   }
-  if (b.n) transpose_batch(c->launch(), b, skip);
+  transpose_batch(c->launch(), b, skip);
 }
 
 // Forward pass (activations only) on B rows of X; logits into Z, then the
-// softmax / cross-entropy kernel (labels optional).  backward: a backward
-// pass or products follow (fp16 pairs: the transposed copies are made too);
-// cache: the pass of a solve's cache rather than of a gradient.
+// softmax / cross-entropy kernel (labels optional).
 void forward_plain(hf_ctx* c, const float* W, const float* X, int B,
-                   const int32_t* y, bool want_delta, bool backward, bool cache) {
+                   const int32_t* y, bool want_delta) {
   const Launch Lc = c->launch();
   c->cat_B = -1;   // the concatenated copy no longer matches the cache
-  transpose_weights(c, W, c->oWT, B, nullptr);
-  if (use_pairs(c, 1, B)) split_input(c, X, B, backward);
-  split_weights(c, W, hf_ctx::K_W, B, backward, nullptr);
+  transpose_weights(c, W, c->oWT, nullptr);
   for (int l = 1; l <= c->L; ++l) {
     const float* Ain = (l == 1) ? X : c->F(c->oA[l - 1]);
     const int ldin = (l == 1) ? c->d[0] : c->ld[l - 1];
+    GemmShape s = shape(B, c->d[l], c->d[l - 1], Ain, nullptr, c->F(c->oWT[l]),
+                        nullptr, ldin, c->ld[l], 1, nullptr);
     EpiArgs e = epi(c, l < c->L);
     e.bias = W + c->offB[l];
     e.out0 = (l < c->L) ? c->F(c->oA[l]) : c->F(c->oZ);
     e.ldo = c->ld[l];
-    e.amax = amax_for(c, l + 1, B);
-    int namax = -1;
-    if (use_pairs(c, l, B)) {
-      GemmShapeS s = shape_s(B, c->d[l], c->d[l - 1], c->ldp[l - 1], c->ldw[l - 1], nullptr);
-      s.yplanes = planes_for(c->d[l - 1]);
-      seg_s(c, s, 0, c->sA[l - 1], c->slot(hf_ctx::K_A, l - 1), Ain, c->sW[l],
-            c->slot(hf_ctx::K_W, l), W + c->offW[l]);
-      s.xr = ldin;
-      s.xk = 1;
-      s.yr = c->d[l - 1];
-      s.yk = 1;
-      namax = sgemm_fwd(Lc, s, e);
-    } else {
-      GemmShape s = shape(B, c->d[l], c->d[l - 1], Ain, nullptr, c->F(c->oWT[l]),
-                          nullptr, ldin, c->ld[l], 1, nullptr);
-      gemm_fwd(Lc, s, e);
-    }
-    if (e.amax)
-      split_tensor(c, c->F(c->oA[l]), B, c->d[l], c->ld[l], c->ldp[l], c->sA[l],
-                   backward ? c->sAT[l] : 0, c->slot(hf_ctx::K_A, l), namax, nullptr);
+    gemm_fwd(Lc, s, e);
   }
   softmax_xent(Lc, c->F(c->oZ), y, B, c->d[c->L], c->ld[c->L], c->F(c->oP),
                want_delta ? c->F(c->oD[c->L]) : nullptr, c->Dp(c->oLoss),
                c->errp());
-  // delta_L: the left operand of the backward GEMM, of the weight gradient's
-  // second term in a Hessian product and of the gradient's, if on pairs
-  const bool tr = cache || pairs_delta_L(c, B);
-  if (want_delta && use_pairs(c, c->L, B) && (tr || c->L > 1))
-    split_tensor(c, c->F(c->oD[c->L]), B, c->d[c->L], c->ld[c->L], c->ldp[c->L], c->sD[c->L],
-                 tr ? c->sDT[c->L] : 0, c->slot(hf_ctx::K_D, c->L), -1, nullptr, tr);
 }
 
 // Backward data pass delta_{l-1} = (delta_l W_l) phi'(A_{l-1}); optionally
 // caches (delta_l W_l) phi''(A_{l-1}) for the Hessian product.
 void backward_data(hf_ctx* c, const float* W, int l, int B, bool cache_e2) {
+  GemmShape s = shape(B, c->d[l - 1], c->d[l], c->F(c->oD[l]), nullptr,
+                      W + c->offW[l], nullptr, c->ld[l], c->d[l - 1], 1, nullptr);
   EpiArgs e = epi(c, 1);
   e.out0 = c->F(c->oD[l - 1]);
   e.out2 = cache_e2 ? c->F(c->oE2[l - 1]) : nullptr;
   e.ldo = c->ld[l - 1];
   e.aux0 = c->F(c->oA[l - 1]);
   e.lda = c->ld[l - 1];
-  e.amax = amax_for(c, l - 1, B);
-  int namax = -1;
-  if (use_pairs(c, l, B)) {
-    GemmShapeS s = shape_s(B, c->d[l - 1], c->d[l], c->ldp[l], c->ldw[l], nullptr);
-    s.yplanes = planes_for(c->d[l]);
-    seg_s(c, s, 0, c->sD[l], c->slot(hf_ctx::K_D, l), c->F(c->oD[l]), c->sWT[l],
-          c->slot(hf_ctx::K_W, l), W + c->offW[l]);
-    s.xr = c->ld[l];
-    s.xk = 1;
-    s.yr = 1;
-    s.yk = c->d[l - 1];
-    namax = sgemm_bwd(c->launch(), s, e);
-  } else {
-    GemmShape s = shape(B, c->d[l - 1], c->d[l], c->F(c->oD[l]), nullptr,
-                        W + c->offW[l], nullptr, c->ld[l], c->d[l - 1], 1, nullptr);
-    gemm_bwd(c->launch(), s, e);
-  }
-  if (e.amax)
-    split_tensor(c, c->F(c->oD[l - 1]), B, c->d[l - 1], c->ld[l - 1], c->ldp[l - 1],
-                 c->sD[l - 1], c->sDT[l - 1], c->slot(hf_ctx::K_D, l - 1), namax, nullptr, true);
+  gemm_bwd(c->launch(), s, e);
 }
 
 // Every layer's weight gradient of a narrow net from one GEMM over the
@@ -1081,58 +769,33 @@ void product_cached(hf_ctx* c, const float* W, const float* X, int B,
   const Launch Lc = c->launch();
   const int L = c->L;
   if (product_narrow(c, W, X, B, v, mode, out, skip)) return;
-  const bool hess = mode == HF_HESSIAN;
-  transpose_weights(c, v, c->oVT, B, skip);
-  split_weights(c, v, hf_ctx::K_V, B, hess, skip);
+  transpose_weights(c, v, c->oVT, skip);
   for (int l = 1; l <= L; ++l) {
+    GemmShape s;
+    if (l == 1) {
+      s = shape(B, c->d[1], c->d[0], X, nullptr, c->F(c->oVT[1]), nullptr,
+                c->d[0], c->ld[1], 1, skip);
+    } else {
+      s = shape(B, c->d[l], c->d[l - 1], c->F(c->oRA[l - 1]), c->F(c->oA[l - 1]),
+                c->F(c->oWT[l]), c->F(c->oVT[l]), c->ld[l - 1], c->ld[l], 2, skip);
+    }
     EpiArgs e = epi(c, l < L);
     e.rbias = v + c->offB[l];
     // RZ_l is read by the softmax R-op (l = L) and by the Hessian's
     // R-backward; the Gauss-Newton product needs only RA_l of a hidden layer
-    e.out1 = (l == L || hess) ? c->F(c->oRZ[l]) : nullptr;
+    e.out1 = (l == L || mode == HF_HESSIAN) ? c->F(c->oRZ[l]) : nullptr;
     e.out2 = (l < L) ? c->F(c->oRA[l]) : nullptr;
     e.ldo = c->ld[l];
     e.aux0 = (l < L) ? c->F(c->oA[l]) : nullptr;
     e.lda = c->ld[l];
-    e.amax = amax_for(c, l + 1, B);
-    int namax = -1;
-    if (use_pairs(c, l, B)) {
-      const int* va = c->slot(hf_ctx::K_V, l);
-      GemmShapeS s = shape_s(B, c->d[l], c->d[l - 1], c->ldp[l - 1], c->ldw[l - 1], skip);
-      s.yplanes = planes_for(c->d[l - 1]);
-      if (l > 1)
-        seg_s(c, s, 0, c->sRA[l - 1], c->slot(hf_ctx::K_RA, l - 1), c->F(c->oRA[l - 1]),
-              c->sW[l], c->slot(hf_ctx::K_W, l), W + c->offW[l]);
-      seg_s(c, s, l > 1, c->sA[l - 1], c->slot(hf_ctx::K_A, l - 1),
-            l > 1 ? c->F(c->oA[l - 1]) : X, c->sV[l], va, v + c->offW[l]);
-      s.xr = l > 1 ? c->ld[l - 1] : c->d[0];
-      s.xk = 1;
-      s.yr = c->d[l - 1];
-      s.yk = 1;
-      namax = sgemm_rfwd(Lc, s, e);
-    } else {
-      GemmShape s;
-      if (l == 1)
-        s = shape(B, c->d[1], c->d[0], X, nullptr, c->F(c->oVT[1]), nullptr,
-                  c->d[0], c->ld[1], 1, skip);
-      else
-        s = shape(B, c->d[l], c->d[l - 1], c->F(c->oRA[l - 1]), c->F(c->oA[l - 1]),
-                  c->F(c->oWT[l]), c->F(c->oVT[l]), c->ld[l - 1], c->ld[l], 2, skip);
-      gemm_rfwd(Lc, s, e);
-    }
-    if (e.amax)
-      split_tensor(c, c->F(c->oRA[l]), B, c->d[l], c->ld[l], c->ldp[l], c->sRA[l],
-                   hess ? c->sRAT[l] : 0, c->slot(hf_ctx::K_RA, l), namax, skip);
+    gemm_rfwd(Lc, s, e);
   }
   softmax_rop(Lc, c->F(c->oP), c->F(c->oRZ[L]), B, c->d[L], c->ld[L],
               c->F(c->oRD[L]), skip);
-  if (use_pairs(c, L, B))
-    split_tensor(c, c->F(c->oRD[L]), B, c->d[L], c->ld[L], c->ldp[L], c->sRD[L], c->sRDT[L],
-                 c->slot(hf_ctx::K_RD, L), -1, skip, true);
   for (int l = L; l >= 1; --l) {
     const float* Ain = (l == 1) ? X : c->F(c->oA[l - 1]);
     const int ldin = (l == 1) ? c->d[0] : c->ld[l - 1];
-    if (hess && l > 1) {
+    if (mode == HF_HESSIAN && l > 1) {
       wgrad(c, l, B, c->F(c->oRD[l]), Ain, c->F(c->oD[l]), c->F(c->oRA[l - 1]),
             ldin, out, skip);
     } else {
@@ -1144,39 +807,18 @@ void product_cached(hf_ctx* c, const float* W, const float* X, int B,
     e.ldo = c->ld[l - 1];
     e.aux0 = c->F(c->oA[l - 1]);
     e.lda = c->ld[l - 1];
-    if (hess) {
-      e.aux1 = c->F(c->oRZ[l - 1]);
-      e.aux2 = c->F(c->oE2[l - 1]);
-    }
-    e.amax = amax_for(c, l - 1, B);
-    int namax = -1;
-    if (use_pairs(c, l, B)) {
-      GemmShapeS s = shape_s(B, c->d[l - 1], c->d[l], c->ldp[l], c->ldw[l], skip);
-      s.yplanes = planes_for(c->d[l]);
-      seg_s(c, s, 0, c->sRD[l], c->slot(hf_ctx::K_RD, l), c->F(c->oRD[l]), c->sWT[l],
-            c->slot(hf_ctx::K_W, l), W + c->offW[l]);
-      if (hess)
-        seg_s(c, s, 1, c->sD[l], c->slot(hf_ctx::K_D, l), c->F(c->oD[l]), c->sVT[l],
-              c->slot(hf_ctx::K_V, l), v + c->offW[l]);
-      s.xr = c->ld[l];
-      s.xk = 1;
-      s.yr = 1;
-      s.yk = c->d[l - 1];
-      namax = hess ? sgemm_rbwd(Lc, s, e) : sgemm_gnbwd(Lc, s, e);
-    } else if (hess) {
+    if (mode == HF_HESSIAN) {
       GemmShape s = shape(B, c->d[l - 1], c->d[l], c->F(c->oRD[l]), c->F(c->oD[l]),
                           W + c->offW[l], v + c->offW[l], c->ld[l], c->d[l - 1],
                           2, skip);
+      e.aux1 = c->F(c->oRZ[l - 1]);
+      e.aux2 = c->F(c->oE2[l - 1]);
       gemm_rbwd(Lc, s, e);
     } else {
       GemmShape s = shape(B, c->d[l - 1], c->d[l], c->F(c->oRD[l]), nullptr,
                           W + c->offW[l], nullptr, c->ld[l], c->d[l - 1], 1, skip);
       gemm_gnbwd(Lc, s, e);
     }
-    if (e.amax)
-      split_tensor(c, c->F(c->oRD[l - 1]), B, c->d[l - 1], c->ld[l - 1], c->ldp[l - 1],
-                   l - 1 > 1 ? c->sRD[l - 1] : 0, c->sRDT[l - 1],
-                   c->slot(hf_ctx::K_RD, l - 1), namax, skip, true);
   }
 }
 
@@ -1548,7 +1190,7 @@ void build_cache(hf_ctx* c, const float* W, const float* X, int B,
   } else if (narrow_build_ok(c, X, v_ext, B)) {
     narrow_build(c, W, X, B, y, hess);
   } else {
-    forward_plain(c, W, X, B, hess ? y : nullptr, hess, true, true);
+    forward_plain(c, W, X, B, hess ? y : nullptr, hess);
     if (hess)
       for (int l = c->L; l >= 2; --l) backward_data(c, W, l, B, true);
     narrow_cache(c, X, B, hess);
@@ -1591,7 +1233,7 @@ void loss_only(hf_ctx* c, const float* W, const float* X, const int32_t* y,
                int B, float* loss, double* loss64) {
   if (c->bf16()) forward_plain_h(c, W, X, B, y, false);
   else if (narrow_build_ok(c, X, nullptr, B)) narrow_build(c, W, X, B, y, false, NARROW_LOSS);
-  else forward_plain(c, W, X, B, y, false, false, false);
+  else forward_plain(c, W, X, B, y, false);
   loss_finalize(c->launch(), c->Dp(c->oLoss), (B + 3) / 4, B, loss, loss64);
 }
 
@@ -1630,7 +1272,7 @@ void loss_grad_any(hf_ctx* c, const float* W, const float* X, const int32_t* y,
     cat_wgrad(c, b, c->F(c->oDcat), nullptr, nullptr, grad, nullptr, nullptr);
     return;
   }
-  forward_plain(c, W, X, b, y, true, true, false);
+  forward_plain(c, W, X, b, y, true);
   loss_finalize(c->launch(), c->Dp(c->oLoss), (b + 3) / 4, b, loss, loss64);
   for (int l = c->L; l >= 1; --l) {
     const float* Ain = (l == 1) ? X : c->F(c->oA[l - 1]);
@@ -1971,10 +1613,8 @@ void hvp_any(hf_ctx* c, const float* W, const float* X, const int32_t* y, int b,
   // grid of fewer than 128 workgroups (half the compute units) would run
   // long K chains on a few units.  The cached route (the forward pass of a
   // solve, then its product) takes 64 x 64 tiles and split K there.
-  // So do nets with layers on fp16 pairs, which have no fused form.
   if (c->cached_layout &&
-      (any_pairs(c, b) ||
-       (long long)((b + 127) / 128) * ((c->d[1] + 127) / 128) < 128)) {
+      (long long)((b + 127) / 128) * ((c->d[1] + 127) / 128) < 128) {
     build_cache(c, W, X, b, y, mode == HF_HESSIAN, v);
     product_cached(c, W, X, b, v, mode, out, nullptr);
     return;

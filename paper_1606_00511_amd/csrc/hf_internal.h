@@ -75,9 +75,6 @@ struct EpiArgs {
   // its capacity in floats; null: never split
   float* split_buf;
   long long split_cap;
-  // GEMMs on fp16 pairs only: partial largest magnitudes (bits) of the
-  // result, for its own split into pairs; null: not wanted
-  uint32_t* amax;
 };
 
 // Output tile (128 or 64 rows and columns) of the single-product GEMMs
@@ -115,90 +112,6 @@ void gemm_wgrad(const Launch& L, const GemmShape& s, const EpiArgs& e);
 // The same with every operand element squared (sum_k X^2 Y^2; bias sums of
 // X[0]^2)
 void gemm_wgrad_sq(const Launch& L, const GemmShape& s, const EpiArgs& e);
-
-// ------------------------------------------------- fp32 GEMMs on fp16 pairs
-// Operands split into two fp16 numbers each (gemm_split.hip).  A value v of
-// a tensor with exponent slot e is stored as v 2^(SPLIT_TOP - e), as 32 hi
-// then 32 lo per 32 consecutive k; leading dimensions count 16-bit elements
-// (2 x K rounded up to 32).  Operands are K-contiguous, with rows up to M
-// (or N) rounded up to 256 and zeros from K to the next multiple of 32.
-constexpr int SPLIT_TOP = 14;              // largest |v| scaled to [2^14, 2^15)
-constexpr int SPLIT_NONFINITE = 0x7fffffff;
-constexpr int SPLIT_WPARTS = 64;           // partials per weight block
-constexpr int SPLIT_CPARTS = 64;           // row chunks of the column maxima
-constexpr int SPLIT_BPARTS = 64;           // most row chunks of a split
-struct GemmShapeS {
-  int M, N, K;
-  const uint16_t* X[2];
-  const uint16_t* Y[2];
-  int ldx, ldy;
-  int nseg;
-  int splits;
-  int yplanes;           // 2, or 3 (weights: their last bits as well)
-  const int* skip;
-  const int* ex[2];      // exponent slots of X[i] and Y[i]
-  const int* ey[2];
-  const int* yc;         // further exponents per row of Y, or null
-  // the fp32 operands, for tensors that cannot be split (infinities, NaN):
-  // X(m, k) = Xf[m * xr + k * xk], Y(n, k) = Yf[n * yr + k * yk]
-  const float* Xf[2];
-  const float* Yf[2];
-  long long xr, xk, yr, yk;
-};
-// The batch-row GEMMs with the epilogues of their fp32 counterparts above;
-// they return how many partials of e.amax they wrote.
-int sgemm_fwd(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-int sgemm_rfwd(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-int sgemm_bwd(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-int sgemm_rbwd(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-int sgemm_gnbwd(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-// Weight gradient as gemm_wgrad, without the bias sums (a SplitJob forms
-// those).
-void sgemm_wgrad(const Launch& L, const GemmShapeS& s, const EpiArgs& e);
-// Output tile (256 or 128) of these GEMMs at the given split along K.
-int split_tile(int M, int N, int splits);
-// One tensor to be split: in is R x C (leading dimension ldi); row and tr
-// (either may be null) get the row-major and the transposed pairs.  amax:
-// namax partial largest magnitudes, from which *slot is set.  cexp: exponents
-// per column that a value is scaled by besides.
-// cpart (the input): namax partial largest magnitudes per column instead of
-// amax; every column is scaled by its own exponent, which cexp receives.
-struct SplitJob {
-  const float* in;
-  int R, C, ldi;
-  uint16_t* row;
-  int ldr, prow;         // leading dimension, planes (2 or 3)
-  uint16_t* tr;
-  int ldt, ptr;
-  uint32_t* amax;
-  int namax;
-  int* slot;
-  int* cexp;
-  const uint32_t* cpart;
-  double* bias;      // column sums: one partial per row chunk and column, or null
-  int chunks;        // split_chunks(R, C)
-};
-struct SplitJobs {
-  static constexpr int MAX = 16;
-  int n;
-  int weights;           // 1: right operands, 2 or 3 planes
-  SplitJob j[MAX];
-};
-// Partial largest magnitudes of R x C values; returns how many (<= 1,024).
-int absmax(const Launch& L, const float* in, int R, int C, int ld, uint32_t* amax,
-           const int* skip);
-// SPLIT_WPARTS partials of every job's tensor (contiguous) into its amax.
-void absmax_weights(const Launch& L, const SplitJobs& js, const int* skip);
-// Partial largest magnitudes per column of R x C values (part: SPLIT_CPARTS x
-// C); *slot = 0.  Returns how many per column.
-int absmax_columns(const Launch& L, const float* in, int R, int C, int ld, uint32_t* part,
-                   int* slot);
-void split(const Launch& L, const SplitJobs& js, const int* skip);
-// Row chunks of a split's grid, at most SPLIT_BPARTS.
-int split_chunks(int R, int C);
-// out[m] = sum over b < nparts of part[b * M + m]
-void bias_sum(const Launch& L, const double* part, int nparts, int M, float* out,
-              const int* skip);
 
 // ------------------------------------------------- narrow-net product
 // The cached curvature product up to the weight gradients in one launch
@@ -423,10 +336,10 @@ struct TransposeBatch {
 };
 void transpose_batch(const Launch& L, const TransposeBatch& b, const int* skip);
 // out[m * ldo + n] = sum_z part[z * M * N + m * N + n] and
-// bout[m] = sum over b < bparts (0: splits) of bpart[b * M + m], both in order
+// bout[m] = sum_z bpart[z * M + m], both in split order
 void splitk_reduce(const Launch& L, const float* part, const double* bpart,
                    int splits, int M, int N, float* out, int ldo, float* bout,
-                   const int* skip, int bparts = 0);
+                   const int* skip);
 
 // ------------------------------------------------------------------- CG
 struct CgState {

@@ -201,14 +201,17 @@ template <int SP>
 __device__ __forceinline__ void splitk_reduce_body(
     const float* __restrict__ part, const double* __restrict__ bpart, int M,
     int N, float* __restrict__ out, int ldo, float* __restrict__ bout, int vec4,
-    int bparts, const int* __restrict__ skip) {
+    const int* __restrict__ skip) {
   if (skip && *skip) return;
   const size_t mn = (size_t)M * N;
   if (bpart) {
     for (int m = blockIdx.x * 256 + threadIdx.x; m < M; m += gridDim.x * 256) {
+      double b[SP];
+#pragma unroll
+      for (int z = 0; z < SP; ++z) b[z] = bpart[(size_t)z * M + m];
       double t = 0.0;
-#pragma unroll 8
-      for (int z = 0; z < bparts; ++z) t += bpart[(size_t)z * M + m];
+#pragma unroll
+      for (int z = 0; z < SP; ++z) t += b[z];
       bout[m] = (float)t;
     }
   }
@@ -250,10 +253,8 @@ __device__ __forceinline__ void splitk_reduce_body(
   extern "C" __global__ __launch_bounds__(256) void hf_splitk_reduce_##SP(    \
       const float* __restrict__ part, const double* __restrict__ bpart,      \
       int M, int N, float* __restrict__ out, int ldo,                        \
-      float* __restrict__ bout, int vec4, int bparts,                        \
-      const int* __restrict__ skip) {                                        \
-    splitk_reduce_body<SP>(part, bpart, M, N, out, ldo, bout, vec4, bparts,  \
-                           skip);                                            \
+      float* __restrict__ bout, int vec4, const int* __restrict__ skip) {    \
+    splitk_reduce_body<SP>(part, bpart, M, N, out, ldo, bout, vec4, skip);   \
   }
 HF_SPLITK_REDUCE(2)
 HF_SPLITK_REDUCE(4)
@@ -362,7 +363,7 @@ void transpose_batch(const Launch& L, const TransposeBatch& b, const int* skip) 
 
 void splitk_reduce(const Launch& L, const float* part, const double* bpart,
                    int splits, int M, int N, float* out, int ldo, float* bout,
-                   const int* skip, int bparts) {
+                   const int* skip) {
   const long long mn = (long long)M * N;
   // the split scratch is 256-byte aligned, so every partial starts 16-byte
   // aligned when N is a multiple of 4
@@ -372,15 +373,13 @@ void splitk_reduce(const Launch& L, const float* part, const double* bpart,
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
   // splits is a power of two from 2 to 32 (the split rules double from 1)
-  void (*k)(const float*, const double*, int, int, float*, int, float*, int, int,
-            const int*) =
+  void (*k)(const float*, const double*, int, int, float*, int, float*, int, const int*) =
       splits == 2 ? hf_splitk_reduce_2 : splits == 4 ? hf_splitk_reduce_4
       : splits == 8 ? hf_splitk_reduce_8 : splits == 16 ? hf_splitk_reduce_16
       : hf_splitk_reduce_32;
   prof_begin(L, "hf_splitk_reduce");
   hipExtLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0,
-                        L.stream, prof_a(L), prof_b(L), 0, part, bpart, M, N, out, ldo, bout, vec4,
-                        bparts ? bparts : splits, skip);
+                        L.stream, prof_a(L), prof_b(L), 0, part, bpart, M, N, out, ldo, bout, vec4, skip);
   prof_end(L, "hf_splitk_reduce", 0.0, 4.0 * mn * (splits + 1));
 }
 

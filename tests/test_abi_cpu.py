@@ -83,6 +83,19 @@ def test_num_params_and_workspace(L, dims):
     assert L.hf_destroy(h) == H.HF_OK
 
 
+@pytest.mark.parametrize("dims,rows,most", [
+    ((440, 2048, 2048, 2048, 2048, 1973), 16384, 5.27e9),
+    ((784, 500, 500, 500, 10), 60000, 2.31e9)])
+def test_workspace_of_the_large_workloads(L, dims, rows, most):
+    """The layers' fp32 buffers (six per hidden layer, five for the output),
+    both transposed weights, the split-K partials and 14 vectors: a program
+    that sets this much aside keeps its rows."""
+    rc, h = create(L, list(dims), max_batch=rows)
+    assert rc == H.HF_OK
+    assert L.hf_workspace_bytes(h, rows) <= most
+    assert L.hf_destroy(h) == H.HF_OK
+
+
 def test_calls_without_workspace_or_with_bad_args(L):
     rc, h = create(L, [8, 6, 4])
     assert rc == H.HF_OK

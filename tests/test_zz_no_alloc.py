@@ -78,6 +78,22 @@ def test_noalloc_matches_hf_hvp(case):
     net.close()
 
 
+def test_noalloc_same_bits_on_a_large_layer():
+    """The grid fills the chip, so hf_hvp runs the fused kernels as well."""
+    import torch
+    from paper_1606_00511_amd import hf as H
+    dims, act, B = (1200, 1600, 300), "tanh", 1300
+    p = WL.make_small(dims, act, B, seed=53)
+    net = H.HFNet(dims, act, B)
+    W, X, y, v = dev(p["theta"]), dev(p["X"]), dev(p["y"]), dev(p["v"])
+    for mode in ("hessian", "gauss_newton"):
+        ref = host(net.hf_hvp(W, X, y, v, mode))
+        out = torch.full((net.n,), float("nan"), device="cuda")
+        assert noalloc(net, W, X, y, v, mode, out) == H.HF_OK
+        assert np.array_equal(host(out), ref)
+    net.close()
+
+
 def test_noalloc_shared_scratch_and_label_flag():
     """Two contexts take turns on the one scratch; a bad label sets the flag
     and the next good call clears it; no workspace is needed."""
