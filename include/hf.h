@@ -369,21 +369,26 @@ const char* hf_build_id(void);
 /*
  * hf_hvp_noalloc: hf_hvp for callers that cannot allocate device memory or
  * hand over a workspace (code under HIP graph capture, tight serving loops,
- * harnesses that forbid allocation).  It computes what hf_hvp computes, with
- * the same kernels, but its scratch is a static device array of
- * HF_NOALLOC_SCRATCH_BYTES per GPU instead of the context's workspace
- * (none needs to be set).  It makes no allocating call (no hipMalloc,
- * hipFree, memset node or host-side device allocation), is asynchronous on
- * the context's stream, and can be captured into a graph.
+ * harnesses that forbid allocation).  It computes what hf_hvp computes, but
+ * its scratch is a static device array of HF_NOALLOC_SCRATCH_BYTES per GPU
+ * instead of the context's workspace (none needs to be set).  It makes no
+ * allocating call (no hipMalloc, hipFree, memset node or host-side device
+ * allocation), is asynchronous on the context's stream, and can be captured
+ * into a graph.  It always runs the kernels that fuse the two forward and the
+ * two backward passes.  So does hf_hvp, with the same bits, except where the
+ * passes of a solve serve a shape better (fp32: fewer than 128 tiles of
+ * 128 x 128 in the first layer; bf16: at least 256 of 256 x 256); there the
+ * two differ by the rounding of sums taken in another order.
  *   label_err  device int32 or NULL: set to 0 by the call, then to 1 if a
  *              label outside [0, d_L) was seen (hf_hvp reports this through
  *              hf_check instead; without label_err it is not reported).
  * The scratch holds the activations, deltas and split-K partials of one
  * product at B rows (less than hf_workspace_bytes(ctx, B), which also
  * holds the solvers' vectors); a batch whose layout needs more than
- * HF_NOALLOC_SCRATCH_BYTES returns HF_EWORKSPACE before any device work.  Every call on one GPU shares that GPU's scratch and leaves
- * its contents there: calls that may overlap on one GPU (other streams,
- * other threads, other contexts) race and must be serialised by the caller.
+ * HF_NOALLOC_SCRATCH_BYTES returns HF_EWORKSPACE before any device work.
+ * Every call on one GPU shares that GPU's scratch and leaves its contents
+ * there: calls that may overlap on one GPU (other streams, other threads,
+ * other contexts) race and must be serialised by the caller.
  * The context's workspace, if any, is not touched.  Other arguments and
  * errors as for hf_hvp; the context's kernel profiler does not time it.
  */

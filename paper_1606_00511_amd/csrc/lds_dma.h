@@ -8,17 +8,19 @@
 
 namespace hfk {
 
+// LDS address of p, which is the same in every lane of the wave.
+__device__ __forceinline__ uint32_t lds_address(void* p) {
+  return __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p);
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane i's bytes
-// land at dst + 16 i (dst is the wave's LDS base, the same in every lane).
+// land at lds_addr + 16 i (the wave's LDS base, the same in every lane).
 // Written as inline assembly: with the compiler builtin, any direct load in
 // flight makes the compiler wait for every outstanding LDS read before each
 // MFMA, which serialises the fragment loads with the MFMAs.  The kernels
 // track these loads themselves (wait_vm before a stage is read).  M0 holds
 // the wave's LDS base and needs one wait state before the load.
-__device__ __forceinline__ uint32_t lds_address(void* p) {
-  return __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p);
-}
 __device__ __forceinline__ void dma16_at(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(src), "s"(lds_addr) : "memory");

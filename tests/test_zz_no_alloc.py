@@ -1,8 +1,8 @@
 """The entry point that allocates nothing (hf_hvp_noalloc), through the C ABI,
 against the existing entry point it varies (hf_hvp) on the same inputs: the
-fp32 bar (rel-L2 <= 1e-4; the two share their kernels and their layout for
-the same batch, so the results are in fact bit-identical) and the bf16-operand
-bar (2e-2).  Two calls in a row, the second with fewer rows, both modes; a
+fp32 bar (rel-L2 <= 1e-4) on grids so small that hf_hvp takes the passes of a
+solve instead of the fused kernels, the same bits where it runs those too, and
+the bf16-operand bar (2e-2).  Two calls in a row, the second with fewer rows, both modes; a
 second context between two calls of the first (the scratch is shared); the
 label flag; and the rejection of a batch whose layout exceeds the scratch,
 before any device work.
