@@ -93,6 +93,23 @@ def test_bf16_curvature_product(case, mode):
     print("%s rel %.2e (bound %.2e)" % (mode, err, bound))
 
 
+@pytest.mark.parametrize("d0,d1,B", [(32, 64, 130), (64, 96, 130), (96, 128, 130),
+                                     (128, 160, 130), (160, 32, 130), (128, 1100, 15000),
+                                     (192, 1100, 15000)])
+def test_bf16_k_block_counts(d0, d1, B):
+    """One to five K blocks of 32 and one to three of 64: fewer, as many as and
+    more than the LDS stages of the fused and the single-product kernels."""
+    dims, act = (d0, d1, 10), "tanh"
+    p = WL.make_small(dims, act, B, seed=303 + d0)
+    h = net(dims, act, B)
+    W, X, y, v = dev(p["theta"]), dev(p["X"]), dev(p["y"]), dev(p["v"])
+    check(host(h.hf_loss_grad(W, X, y)[1]),
+          O.loss_grad(dims, act, p["theta"], p["X"], p["y"])[1], act, tol=TOL)
+    for mode in ("hessian", "gauss_newton"):
+        check(host(h.hf_hvp(W, X, y, v, mode)),
+              O.curvature(dims, act, p["theta"], p["X"], p["y"], p["v"], mode), act, tol=TOL)
+
+
 def test_bf16_cached_product_matches_stateless():
     """The solve's cached product path against the stateless one: with no
     damping the first CG iterate is x_1 = -(g.g / g.A g) g, where A g is
